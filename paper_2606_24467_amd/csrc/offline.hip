@@ -20,79 +20,109 @@ struct SrhArgs {
   int32_t S, N, H, L;
 };
 
-constexpr int kSrhHeads = 4;        // heads per workgroup
-constexpr int kSrhSplit = 4;        // waves per head
-constexpr int kSrhBatch = 8;        // answer steps whose span loads a wave issues together
+constexpr int kSrhHeads = 2;        // heads per workgroup
+constexpr int kSrhSplit = 8;        // waves per head
+constexpr int kSrhBatch = 16;       // answer steps whose span loads a wave issues together
 constexpr int kSrhPairs = 2048;     // (sample, step) pairs tested per pass
 
-// A workgroup of 16 waves covers 4 consecutive heads.  Per block of (sample,
-// step) pairs it first records in LDS whether each step generated one of its
-// span's tokens (one thread per pair, looping over the span); the four
-// waves of a head then take every fourth answer step of the block, load
-// kSrhBatch spans together, sum each over the span (lanes over positions,
-// then a fixed butterfly) and accumulate the step sums in fp64 in step
-// order.  The four waves' totals are added in wave order, so the result does
-// not depend on scheduling.
+// Bound by latency (a few answer steps per head, each a short run of a row of
+// its own), so every chain is kept short.  A workgroup of 16 waves covers 2
+// consecutive heads; two workgroups fit a CU.  Per block of (sample, step)
+// pairs:
+//   - each pair is tested by as many lanes as 1024 threads give it (1 to 64),
+//     strided over the span's tokens, and joined by a ballot;
+//   - the answer steps are listed in LDS in step order (ballot, popcount and
+//     a prefix over the 64-pair chunks);
+//   - the eight waves of a head take every eighth entry of the list, load 16
+//     spans together (lanes over positions) and add them per lane in fp64 in
+//     list order: one butterfly per head and wave at the end.
+// At 4 samples x 32 steps x 1024 heads with 32-token spans the call (with the
+// set selection) takes 23.9 us; one thread per pair, an unlisted walk over the
+// pairs, 8 spans a batch and a butterfly per step took 38.5 us.
+// The waves' totals are added in wave order, so the result does not depend on
+// scheduling.
 __global__ __launch_bounds__(64 * kSrhHeads * kSrhSplit) void srh_score_kernel(const SrhArgs a) {
-  constexpr int NW = kSrhHeads * kSrhSplit;
-  __shared__ unsigned char hit_s[kSrhPairs];
+  constexpr int NW = kSrhHeads * kSrhSplit, NT = 64 * NW, CH = kSrhPairs / 64;
+  static_assert(kSrhPairs % 64 == 0, "whole 64-pair chunks");
+  __shared__ int a0_s[kSrhPairs], n_s[kSrhPairs];   // span of each pair; length 0: no answer step
+  __shared__ uint16_t list_s[kSrhPairs];            // the block's answer steps, ascending
+  __shared__ int cnt_s[CH];                         // answer steps per 64-pair chunk
   __shared__ double part_s[NW];
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int h = blockIdx.x * kSrhHeads + wave / kSrhSplit, sub = wave % kSrhSplit;
   const int SN = a.S * a.N;
   double acc = 0.0;
   for (int p0 = 0; p0 < SN; p0 += kSrhPairs) {
     const int np = min(kSrhPairs, SN - p0);
-    for (int q = (int)threadIdx.x; q < np; q += 64 * NW) {
-      const int p = p0 + q, s = p / a.N;
-      const int a0 = a.spans[2 * s], n = a.spans[2 * s + 1];
-      const int32_t y = a.gen[p];
-      const int32_t *tok = a.ctx + (int64_t)s * a.L + a0;
+    int lpp = 1;                                    // lanes per pair, a power of two
+    while (lpp < 64 && 2 * lpp * np <= NT) lpp *= 2;
+    const int sl = lane & (lpp - 1), lane0 = lane - sl;
+    const uint64_t group = (lpp == 64 ? ~0ull : (1ull << lpp) - 1) << lane0;
+    for (int qb = 0; qb < np; qb += NT / lpp) {     // uniform: every lane takes part in the ballot
+      const int q = qb + tid / lpp;
+      int a0 = 0, n = 0;
       bool hit = false;
-      for (int j = 0; j < n; ++j) hit |= (tok[j] == y);
-      hit_s[q] = hit ? 1 : 0;
+      if (q < np) {
+        const int p = p0 + q, s = p / a.N;
+        const int32_t y = a.gen[p];
+        a0 = a.spans[2 * s];
+        n = a.spans[2 * s + 1];
+        const int32_t *tok = a.ctx + (int64_t)s * a.L + a0;
+        for (int j = sl; j < n; j += lpp) hit |= (tok[j] == y);
+      }
+      const bool any = (__ballot(hit) & group) != 0;
+      if (q < np && sl == 0) {
+        a0_s[q] = a0;
+        n_s[q] = any ? n : 0;
+      }
     }
     __syncthreads();
+    for (int ch = wave; ch < CH; ch += NW) {
+      const int q = 64 * ch + lane;
+      const uint64_t m = __ballot(q < np && n_s[q] > 0);
+      if (lane == 0) cnt_s[ch] = __popcll(m);
+    }
+    __syncthreads();
+    int nh = 0;                                     // answer steps of the block
+    for (int ch = 0; 64 * ch < np; ++ch) {
+      if (ch % NW == wave) {
+        const int q = 64 * ch + lane;
+        const bool hit = q < np && n_s[q] > 0;
+        const uint64_t m = __ballot(hit);
+        if (hit) list_s[nh + __popcll(m & ((1ull << lane) - 1))] = (uint16_t)q;
+      }
+      nh += cnt_s[ch];
+    }
+    nh = __builtin_amdgcn_readfirstlane(nh);
+    __syncthreads();
     if (h < a.H) {
-      int q = sub;
-      for (;;) {
-        // the wave's next kSrhBatch answer steps of the block (uniform)
-        int qb[kSrhBatch], nb = 0;
-        while (nb < kSrhBatch && q < np) {
-          if (hit_s[q]) qb[nb++] = q;
-          q += kSrhSplit;
-        }
-        if (nb == 0) break;
+      for (int i0 = sub; i0 < nh; i0 += kSrhSplit * kSrhBatch) {
         const float *row[kSrhBatch];
         int len[kSrhBatch], nmax = 0;
 #pragma unroll
         for (int b = 0; b < kSrhBatch; ++b) {
-          const int p = p0 + (b < nb ? qb[b] : qb[0]), s = p / a.N;
-          const int a0 = a.spans[2 * s];
-          len[b] = b < nb ? a.spans[2 * s + 1] : 0;
-          row[b] = a.attn + ((int64_t)p * a.H + h) * (int64_t)a.L + a0;
+          const int i = i0 + kSrhSplit * b;
+          const int q = __builtin_amdgcn_readfirstlane((int)list_s[min(i, nh - 1)]);
+          const int n = __builtin_amdgcn_readfirstlane(n_s[q]);
+          const int a0 = __builtin_amdgcn_readfirstlane(a0_s[q]);
+          len[b] = i < nh ? n : 0;
+          row[b] = a.attn + ((int64_t)(p0 + q) * a.H + h) * (int64_t)a.L + a0;
           nmax = max(nmax, len[b]);
         }
-        float v[kSrhBatch];
-#pragma unroll
-        for (int b = 0; b < kSrhBatch; ++b) v[b] = 0.f;
-        for (int j = lane; j < nmax; j += 64) {
+        for (int j0 = 0; j0 < nmax; j0 += 64) {
+          const int j = j0 + lane;
           float x[kSrhBatch];
 #pragma unroll
           for (int b = 0; b < kSrhBatch; ++b) x[b] = (j < len[b]) ? row[b][j] : 0.f;
 #pragma unroll
-          for (int b = 0; b < kSrhBatch; ++b) v[b] += x[b];
-        }
-#pragma unroll
-        for (int b = 0; b < kSrhBatch; ++b) {
-#pragma unroll
-          for (int o = 32; o >= 1; o >>= 1) v[b] += __shfl_xor(v[b], o);
-          if (b < nb) acc += (double)v[b];
+          for (int b = 0; b < kSrhBatch; ++b) acc += (double)x[b];
         }
       }
     }
-    __syncthreads();   // hit_s is rewritten by the next block
+    __syncthreads();   // the spans and the list are rewritten by the next block
   }
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) acc += __shfl_xor(acc, o);
   if (lane == 0) part_s[wave] = acc;
   __syncthreads();
   if (sub == 0 && lane == 0 && h < a.H) {

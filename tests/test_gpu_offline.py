@@ -79,6 +79,22 @@ def test_srh_scores_match_oracle(gpu, S, N, H, Lc):
     np.testing.assert_allclose(got, want, rtol=SRH_RTOL, atol=1e-6)
 
 
+# pairs at the edges of the lanes a pair gets (1024 threads over the block's pairs) and of
+# a block of 2048; spans past 64 positions and heads left over in the last workgroup
+@pytest.mark.parametrize("S,N,H,Lc,span", [(1, 16, 3, 300, 200), (1, 17, 3, 300, 64),
+                                           (2, 512, 5, 90, 65), (1, 1025, 3, 90, 3),
+                                           (1, 2048, 3, 60, 9), (1, 2049, 3, 60, 9)])
+def test_srh_scores_answer_step_list(gpu, S, N, H, Lc, span):
+    """fp64 sums over steps and positions, rounded once: half an fp32 ulp
+    (6e-8 relative) from the oracle, allowed twice."""
+    _say(f"case srh list S={S} N={N} H={H} L={Lc} span={span}")
+    attn, gen, ctx, spans = _calibration(S * 1000 + N, S, N, H, Lc, max_span=span)
+    spans[0, 0], spans[0, 1] = min(spans[0, 0], Lc - span), span
+    gen[0, -1] = ctx[0, spans[0, 0] + span - 1]      # the last step answers with the last token
+    got = _run(gpu, attn, gen, ctx, spans)
+    np.testing.assert_allclose(got, OO.srh_scores(attn, gen, ctx, spans), rtol=1.2e-7)
+
+
 def test_select_srh_matches_oracle_with_ties(gpu):
     rng = np.random.default_rng(5)
     n_layers, hp = 32, 32
