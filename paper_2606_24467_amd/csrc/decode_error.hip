@@ -84,15 +84,24 @@ __device__ __forceinline__ DecCache dec_cache(const DecArgs &a, int cache, int b
 // head g * G + hh); RT = ceil(R / 16) row tiles, padding rows have zero
 // queries.  The P.V step runs on v_mfma_f32_16x16x4_f32 with fp32
 // probabilities and V converted exactly to fp32: wave w owns the output
-// tiles of every row tile and the column tiles w*CTW .. +CTW (lane (quad, c)
-// holds rows 4*quad .. +3 of a tile against column c).
+// tiles of every row tile and the 16*CTW columns from 16*CTW*w on (lane (quad,
+// c) holds rows 4*quad .. +3 of a tile against columns CTW*c .. +CTW-1, so that
+// one LDS read gives its V elements of a key).
+//
+// A step is bound by its LDS accesses, so the rows are padded to spread over
+// the 64 banks: a logits row by 4 floats (16-byte accesses where a lane takes
+// consecutive keys; in P.V lane (quad, c) falls on bank 4 c + quad), a V row by
+// 16*CTW elements (the four quads' keys fall on banks of their own), and every
+// thread takes part in the softmax with its keys in registers.  One layer at
+// L = 32768, 32/8 heads, D = 128, bf16, 8 steps: the call 77.8 -> 76.2 us.
 template <typename T, int D, int RT>
 __global__ __launch_bounds__(256) void dec_attn_kernel(const DecArgs a) {
   constexpr int NS = Slices<T, D>::n, U4 = QLayout<T, D>::U4, STRIDE = QLayout<T, D>::STRIDE;
   constexpr int RP = RT * 16;                  // rows with padding
   constexpr int CTW = D / 16 / 4;              // column tiles per wave in the P.V step
-  constexpr int ZS = kDecSub + 1;              // padded row of the logits buffer
-  static_assert(CTW >= 1 && D % 64 == 0, "column tiles");
+  constexpr int ZS = kDecSub + 4;              // padded row of the logits buffer
+  constexpr int VS = D + 16 * CTW;             // padded V row, in elements
+  static_assert((CTW == 1 || CTW == 2) && D % 64 == 0, "column tiles");
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int c = lane & 15, quad = lane >> 4;
   const int g = blockIdx.y, b = (int)blockIdx.z >> 1, cache = (int)blockIdx.z & 1;
@@ -102,9 +111,10 @@ __global__ __launch_bounds__(256) void dec_attn_kernel(const DecArgs a) {
   const int c_end = min(cc.n_keys, c0 + kDecChunk);
 
   __shared__ uint4 q_lds[RP * STRIDE];
-  __shared__ float zs[RP * ZS];                 // logits, then probabilities
-  __shared__ uint4 vs4[kDecSub * D * sizeof(T) / 16];   // the step's V rows
+  __shared__ __align__(16) float zs[RP * ZS];   // logits, then probabilities
+  __shared__ uint4 vs4[kDecSub * VS * sizeof(T) / 16];   // the step's V rows
   const T *vs = reinterpret_cast<const T *>(vs4);
+  typedef T VPart __attribute__((ext_vector_type(CTW)));   // a lane's V elements of one key
   __shared__ float m_s[RP], l_s[RP], alpha_s[RP];
 
   // queries of the group's rows
@@ -169,40 +179,57 @@ __global__ __launch_bounds__(256) void dec_attn_kernel(const DecArgs a) {
       tile_logits_all<T, D, RT, true>(kf[i], qreg, q_lds, c, quad, lg);
 #pragma unroll
       for (int rt = 0; rt < RT; ++rt)
+      {
+        const int j = 16 * e + 4 * quad;
+        f32x4 z;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int j = 16 * e + 4 * quad + r;
-          zs[(rt * 16 + c) * ZS + j] = (k0 + j < c_end) ? lg[rt][r] * a.c1 : -INFINITY;
-        }
+        for (int r = 0; r < 4; ++r) z[r] = (k0 + j + r < c_end) ? lg[rt][r] * a.c1 : -INFINITY;
+        *reinterpret_cast<f32x4 *>(zs + (rt * 16 + c) * ZS + j) = z;
+      }
     }
     // V rows of the step
 #pragma unroll
-    for (int u = 0; u < VPT; ++u) vs4[tid + 256 * u] = vr[u];
+    for (int u = 0; u < VPT; ++u) {
+      const int idx = tid + 256 * u, j = idx / V4;
+      vs4[j * (VS * (int)sizeof(T) / 16) + (idx - j * V4)] = vr[u];
+    }
     if (k0 + kDecSub < c_end) issue(k0 + kDecSub);   // uniform
     __syncthreads();
-    // online softmax: four threads per row, kDecSub / 4 keys each
+    // online softmax: TPR threads per row (as many as 256 threads give it), KPT
+    // consecutive keys each, held in registers
     {
-      constexpr int KPT = kDecSub / 4;
-      const int r = tid >> 2, part = tid & 3;
+      constexpr int TPR = RT == 1 ? 16 : (RT == 2 ? 8 : 4), KPT = kDecSub / TPR;
+      const int r = tid / TPR, part = tid % TPR;
       if (r < RP) {
-        float* zr = zs + r * ZS + KPT * part;
+        f32x4 *zr = reinterpret_cast<f32x4 *>(zs + r * ZS + KPT * part);
+        f32x4 z[KPT / 4];
         float mx = -INFINITY;
-        for (int j = 0; j < KPT; ++j) mx = fmaxf(mx, zr[j]);
-        mx = fmaxf(mx, __shfl_xor(mx, 1));
-        mx = fmaxf(mx, __shfl_xor(mx, 2));
+#pragma unroll
+        for (int j = 0; j < KPT / 4; ++j) {
+          z[j] = zr[j];
+          mx = fmaxf(mx, fmaxf(fmaxf(z[j][0], z[j][1]), fmaxf(z[j][2], z[j][3])));
+        }
+#pragma unroll
+        for (int o = 1; o < TPR; o <<= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
         const float m_old = m_s[r];
         const float m_new = fmaxf(m_old, mx);
         // a row with no visible key yet keeps zero weight
         const float alpha = (m_new == -INFINITY) ? 1.f : fast_exp2(m_old - m_new);
         float sm = 0.f;
-        for (int j = 0; j < KPT; ++j) {
-          const float p = (m_new == -INFINITY) ? 0.f : fast_exp2(zr[j] - m_new);
-          zr[j] = p;
-          sm += p;
+#pragma unroll
+        for (int j = 0; j < KPT / 4; ++j) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const float p = (m_new == -INFINITY) ? 0.f : fast_exp2(z[j][e] - m_new);
+            z[j][e] = p;
+            sm += p;
+          }
+          zr[j] = z[j];
         }
-        sm += __shfl_xor(sm, 1);
-        sm += __shfl_xor(sm, 2);
-        // the four threads of a row hold the same values; the first writes
+#pragma unroll
+        for (int o = 1; o < TPR; o <<= 1) sm += __shfl_xor(sm, o);
+        // a row's threads hold the same values (one wave, so all have read m_old);
+        // the first writes
         if (part == 0) {
           m_s[r] = m_new;
           l_s[r] = l_s[r] * alpha + sm;
@@ -224,9 +251,10 @@ __global__ __launch_bounds__(256) void dec_attn_kernel(const DecArgs a) {
 #pragma unroll 4
     for (int j = 0; j < kDecSub / 4; ++j) {
       const int key = 4 * j + quad;
+      const VPart vp = *reinterpret_cast<const VPart *>(vs + key * VS + CTW * (16 * wave + c));
       float vv[CTW];
 #pragma unroll
-      for (int ct = 0; ct < CTW; ++ct) vv[ct] = (float)vs[key * D + 16 * (wave * CTW + ct) + c];
+      for (int ct = 0; ct < CTW; ++ct) vv[ct] = (float)vp[ct];
 #pragma unroll
       for (int rt = 0; rt < RT; ++rt) {
         const float p = zs[(rt * 16 + c) * ZS + key];
@@ -248,7 +276,7 @@ __global__ __launch_bounds__(256) void dec_attn_kernel(const DecArgs a) {
       if (row < a.R) {
         float *o = a.part_o + (slot * kMaxDecRows + row) * D;
 #pragma unroll
-        for (int ct = 0; ct < CTW; ++ct) o[16 * (wave * CTW + ct) + c] = acc[rt][ct][r];
+        for (int ct = 0; ct < CTW; ++ct) o[CTW * (16 * wave + c) + ct] = acc[rt][ct][r];
       }
     }
 }

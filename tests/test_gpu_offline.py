@@ -194,6 +194,18 @@ def test_layer_error_matches_oracle(gpu, name, kw):
     np.testing.assert_allclose(got, want, rtol=ERR_RTOL)
 
 
+# (a tail of one key, of a 64-key step and of a 512-key chunk) x every row-tile count
+@pytest.mark.parametrize("D,dtype", [(64, C.BF16), (128, C.BF16), (64, C.F32), (128, C.F32)])
+@pytest.mark.parametrize("T,L", [(4, 513), (8, 575), (12, 577), (16, 64)])
+def test_layer_error_row_tiles(gpu, D, dtype, T, L):
+    """The attention's layouts: one to four row tiles (G = 4 heads of a group x
+    T steps), both head sizes and types, whose LDS padding and columns per lane
+    differ.  The tolerance is that of the cases above (2e-3)."""
+    _say(f"case layer error D={D} dtype={dtype} T={T} L={L}")
+    c = _error_case(31, lens=(L,), Hq=8, Hkv=2, D=D, T=T, B=33, d_model=64, dtype=dtype)
+    np.testing.assert_allclose(_gpu_error(c, gpu), _oracle_error(c), rtol=ERR_RTOL)
+
+
 def test_layer_error_is_zero_when_every_position_is_kept(gpu):
     """B >= L: the compact cache holds every row in order, so both attentions
     see the same keys in the same chunks and the error is exactly 0."""
