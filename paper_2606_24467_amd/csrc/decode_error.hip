@@ -7,7 +7,8 @@
 //                       the group's rows (decoding step x query head of the
 //                       group) against one 512-key chunk, QK^T on MFMA, online
 //                       softmax in LDS, P.V on fp32 MFMA; partial (max, sum, O)
-//   dec_combine_kernel  merges the chunks of every row into A (fp32)
+//   dec_combine_kernel  merges the chunks of every row into A_full and
+//                       A_full - A_comp (fp32)
 //   dec_proj_kernel     y = W_O x for x = A_full and A_full - A_comp on fp32
 //                       MFMA (16 rows of W_O per workgroup, 16 waves on
 //                       sixteenths of its columns); per-workgroup sums of y^2
@@ -22,6 +23,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 #include "../../include/compresskv_offline.h"
 #include "api_common.h"
@@ -45,7 +47,7 @@ struct DecArgs {
   const int32_t *cu;
   float2 *part_ml;               // [2][batch][Hkv][n_chunks][64] (max, sum), log2 domain
   float *part_o;                 // [2][batch][Hkv][n_chunks][64][D]
-  float *a;                      // [2][batch][T][Hq][D]
+  float *a;                      // [2][batch][T][Hq][D]: A_full, A_full - A_comp
   int64_t k_st, k_sh, v_st, v_sh;
   int T, Hq, Hkv, G, B, batch, R, n_chunks;
   int b0, t0, q_T;               // the block's first sequence and step; steps in q
@@ -281,52 +283,60 @@ __global__ __launch_bounds__(256) void dec_attn_kernel(const DecArgs a) {
     }
 }
 
-// Grid (R, Hkv, batch * 2), D threads: A of row r of the group from its
-// chunks.  The chunk maxima and weights are formed in parallel (LDS), the
-// weighted sums run over the chunks in order (thread d: column d).
+// Grid (R, Hkv, batch), 2 * D threads: A of row r of the group from its
+// chunks, the first D threads on the full cache and the others on the compact
+// one; written as A_full and A_full - A_comp, so that the projection, whose
+// every workgroup reads all of it, does not form the difference anew.  The
+// chunk maxima and weights are formed in parallel (LDS), the weighted sums run
+// over the chunks in order (thread d of a half: column d).
 template <int D>
-__global__ __launch_bounds__(D) void dec_combine_kernel(const DecArgs a) {
+__global__ __launch_bounds__(2 * D) void dec_combine_kernel(const DecArgs a) {
   constexpr int kMaxCh = 1024;   // chunks per pass of the weight table
-  __shared__ float w_s[kMaxCh];
-  __shared__ float red[D];
-  const int r = blockIdx.x, g = blockIdx.y, b = (int)blockIdx.z >> 1, cache = (int)blockIdx.z & 1;
-  const int d = threadIdx.x;
+  __shared__ float w_s[2][kMaxCh];
+  __shared__ float red[2][D];
+  const int r = blockIdx.x, g = blockIdx.y, b = blockIdx.z;
+  const int cache = (int)threadIdx.x / D, d = (int)threadIdx.x % D;
   const int L = a.cu[a.b0 + b + 1] - a.cu[a.b0 + b];
   const int n_keys = cache == 0 ? L : min(L, a.B);
   const int nch = (n_keys + kDecChunk - 1) / kDecChunk;
+  const int nch_full = (L + kDecChunk - 1) / kDecChunk;   // >= nch: bounds the loops with barriers
   const int64_t slot0 = (((int64_t)cache * a.batch + b) * a.Hkv + g) * a.n_chunks;
   // the row's maximum over its chunks: per thread over chunks d, d + D, ...,
   // then a tree in LDS (max is exact in any order)
   float M = -INFINITY;
   for (int ch = d; ch < nch; ch += D) M = fmaxf(M, a.part_ml[(slot0 + ch) * kMaxDecRows + r].x);
-  red[d] = M;
+  red[cache][d] = M;
   __syncthreads();
   for (int h = D / 2; h > 0; h >>= 1) {
-    if (d < h) red[d] = fmaxf(red[d], red[d + h]);
+    if (d < h) red[cache][d] = fmaxf(red[cache][d], red[cache][d + h]);
     __syncthreads();
   }
-  M = red[0];
+  M = red[cache][0];
   float lsum = 0.f, o = 0.f;
-  for (int c0 = 0; c0 < nch; c0 += kMaxCh) {
-    const int n = min(kMaxCh, nch - c0);
+  for (int c0 = 0; c0 < nch_full; c0 += kMaxCh) {
+    const int n = min(kMaxCh, nch - c0);   // <= 0 past the compact cache's chunks
     __syncthreads();
     for (int ch = d; ch < n; ch += D)
-      w_s[ch] = fast_exp2(a.part_ml[(slot0 + c0 + ch) * kMaxDecRows + r].x - M);
+      w_s[cache][ch] = fast_exp2(a.part_ml[(slot0 + c0 + ch) * kMaxDecRows + r].x - M);
     __syncthreads();
     const float *po = a.part_o + ((slot0 + c0) * kMaxDecRows + r) * D + d;
 #pragma unroll 8
-    for (int ch = 0; ch < n; ++ch) o += po[(int64_t)ch * kMaxDecRows * D] * w_s[ch];
+    for (int ch = 0; ch < n; ++ch) o += po[(int64_t)ch * kMaxDecRows * D] * w_s[cache][ch];
     // every thread forms the same sum of the chunk sums, in chunk order
     for (int ch = 0; ch < n; ++ch)
-      lsum += a.part_ml[(slot0 + c0 + ch) * kMaxDecRows + r].y * w_s[ch];
+      lsum += a.part_ml[(slot0 + c0 + ch) * kMaxDecRows + r].y * w_s[cache][ch];
   }
+  const float out = o / lsum;
+  red[cache][d] = out;
+  __syncthreads();
   const int t = r / a.G, h = g * a.G + (r - t * a.G);
-  a.a[((((int64_t)cache * a.batch + b) * a.T + t) * a.Hq + h) * D + d] = o / lsum;
+  a.a[((((int64_t)cache * a.batch + b) * a.T + t) * a.Hq + h) * D + d] =
+      cache == 0 ? out : red[0][d] - out;
 }
 
 struct ProjArgs {
   const char *w_o;          // [d_model][HD], dtype T
-  const float *a;           // [2][NV][HD]: A_full, A_comp
+  const float *a;           // [2][NV][HD]: A_full, A_full - A_comp
   float *part_ss;           // [n_wg][2][kMaxVectors]: sums of y_full^2, y_diff^2 over the
                             // workgroup's rows of W_O
   int d_model, HD, NV;
@@ -347,42 +357,34 @@ __global__ __launch_bounds__(64 * kProjWaves) void dec_proj_kernel(const ProjArg
   const int o = (int)blockIdx.x * kProjRows + c;            // this lane's row of W_O
   const bool o_ok = o < p.d_model;
   const T *wr = reinterpret_cast<const T *>(p.w_o) + (int64_t)(o_ok ? o : 0) * p.HD;
-  const float *xf[XT], *xc[XT];
-  int kind[XT];
+  const float *xr[XT];
+  bool x_ok[XT];
 #pragma unroll
   for (int x = 0; x < XT; ++x) {
     const int n = 16 * x + c;                                 // this lane's row of X tile x
-    kind[x] = n < p.NV ? 0 : (n < 2 * p.NV ? 1 : 2);          // full, difference, padding
-    const int v = kind[x] == 0 ? n : (kind[x] == 1 ? n - p.NV : 0);
-    xf[x] = p.a + (int64_t)v * p.HD;
-    xc[x] = p.a + (int64_t)(p.NV + v) * p.HD;
+    x_ok[x] = n < 2 * p.NV;                                   // else padding
+    xr[x] = p.a + (int64_t)(x_ok[x] ? n : 0) * p.HD;
   }
   f32x4 acc[XT];
 #pragma unroll
   for (int x = 0; x < XT; ++x) acc[x] = f32x4{0.f, 0.f, 0.f, 0.f};
   const int qw = p.HD / kProjWaves;                           // columns per wave
   const int k_end = (wave + 1) * qw;
-  // X tile x's four floats at column k (row as set above), the difference
-  // rows formed here
+  // X tile x's four floats at column k (row as set above)
   auto x_at = [&](int x, int k) {
-    float4 xv = *reinterpret_cast<const float4 *>(xf[x] + k);
-    if (kind[x] == 1) {
-      const float4 y = *reinterpret_cast<const float4 *>(xc[x] + k);
-      xv = make_float4(xv.x - y.x, xv.y - y.y, xv.z - y.z, xv.w - y.w);
-    } else if (kind[x] == 2) {
-      xv = make_float4(0.f, 0.f, 0.f, 0.f);
-    }
-    return xv;
+    const float4 xv = *reinterpret_cast<const float4 *>(xr[x] + k);
+    return x_ok[x] ? xv : make_float4(0.f, 0.f, 0.f, 0.f);
   };
-  auto w_at = [&](int k) {   // four elements of this lane's row of W_O at column k
+  // four elements of this lane's row of W_O at column k, as stored
+  using WRaw = std::conditional_t<sizeof(T) == 2, uint2, float4>;
+  auto w_raw = [&](int k) { return *reinterpret_cast<const WRaw *>(wr + k); };
+  auto w_val = [&](WRaw raw) {
     float4 wv;
-    if constexpr (sizeof(T) == 2) {
-      const uint2 raw = *reinterpret_cast<const uint2 *>(wr + k);
+    if constexpr (sizeof(T) == 2)
       wv = make_float4(__uint_as_float(raw.x << 16), __uint_as_float(raw.x & 0xFFFF0000u),
                        __uint_as_float(raw.y << 16), __uint_as_float(raw.y & 0xFFFF0000u));
-    } else {
-      wv = *reinterpret_cast<const float4 *>(wr + k);
-    }
+    else
+      wv = raw;
     return o_ok ? wv : make_float4(0.f, 0.f, 0.f, 0.f);
   };
   // 64 columns per trip: lane (quad, c) takes the 16 consecutive columns
@@ -390,23 +392,36 @@ __global__ __launch_bounds__(64 * kProjWaves) void dec_proj_kernel(const ProjArg
   // and of its X rows, four MFMA steps of 4 columns each (the products are
   // summed over the columns, so which 4 columns a step takes is free as long
   // as W_O and X agree)
+  // W_O is the stream from HBM: its loads run one trip ahead.  With that and
+  // the difference rows read ready-made (a third less from L2 per workgroup)
+  // the error call at L = 32768, 32/8 heads, D = 128, d_model = 4096, bf16, 8
+  // steps takes 71.9 us, before 76.2.
   int k0 = wave * qw;
+  WRaw wn[4] = {};
+  if (k0 + 64 <= k_end) {
+#pragma unroll
+    for (int st = 0; st < 4; ++st) wn[st] = w_raw(k0 + 16 * quad + 4 * st);
+  }
   for (; k0 + 64 <= k_end; k0 += 64) {
     const int kq = k0 + 16 * quad;
-    float4 wv[4];
+    WRaw wc[4];
 #pragma unroll
-    for (int st = 0; st < 4; ++st) wv[st] = w_at(kq + 4 * st);
+    for (int st = 0; st < 4; ++st) wc[st] = wn[st];
+    if (k0 + 128 <= k_end) {
+#pragma unroll
+      for (int st = 0; st < 4; ++st) wn[st] = w_raw(kq + 64 + 4 * st);
+    }
 #pragma unroll
     for (int x = 0; x < XT; ++x) {
 #pragma unroll
       for (int st = 0; st < 4; ++st)
         acc[x] = mfma_slice<float>(__builtin_bit_cast(uint4, x_at(x, kq + 4 * st)),
-                                   __builtin_bit_cast(uint4, wv[st]), acc[x]);
+                                   __builtin_bit_cast(uint4, w_val(wc[st])), acc[x]);
     }
   }
   // the rest in steps of 16 columns (lane quad on columns k0 + 4 quad .. + 3)
   for (; k0 < k_end; k0 += 16) {
-    const float4 wv = w_at(k0 + 4 * quad);
+    const float4 wv = w_val(w_raw(k0 + 4 * quad));
 #pragma unroll
     for (int x = 0; x < XT; ++x)
       acc[x] = mfma_slice<float>(__builtin_bit_cast(uint4, x_at(x, k0 + 4 * quad)),
@@ -476,7 +491,8 @@ static void launch_dec_t(const DecArgs &a, const ProjArgs &pa, int rt, int n_wg,
     case 3: hipLaunchKernelGGL((dec_attn_kernel<T, D, 3>), g1, dim3(256), 0, s, a); break;
     default: hipLaunchKernelGGL((dec_attn_kernel<T, D, 4>), g1, dim3(256), 0, s, a); break;
   }
-  hipLaunchKernelGGL((dec_combine_kernel<D>), dim3(a.R, a.Hkv, a.batch * 2), dim3(D), 0, s, a);
+  hipLaunchKernelGGL((dec_combine_kernel<D>), dim3(a.R, a.Hkv, a.batch), dim3(2 * D), 0, s,
+                     a);
   switch ((2 * pa.NV + 15) / 16) {
     case 1: hipLaunchKernelGGL((dec_proj_kernel<T, 1>), dim3(n_wg), dim3(64 * kProjWaves), 0, s, pa); break;
     case 2: hipLaunchKernelGGL((dec_proj_kernel<T, 2>), dim3(n_wg), dim3(64 * kProjWaves), 0, s, pa); break;
