@@ -22,23 +22,35 @@ struct SrhArgs {
 
 constexpr int kSrhHeads = 2;        // heads per workgroup
 constexpr int kSrhSplit = 8;        // waves per head
-constexpr int kSrhBatch = 16;       // answer steps whose span loads a wave issues together
+constexpr int kSrhBatch = 8;        // answer steps whose span loads a wave issues together
+constexpr int kSrhTokens = 8;       // span tokens whose loads a lane of the test issues together
 constexpr int kSrhPairs = 2048;     // (sample, step) pairs tested per pass
 
 // Bound by latency (a few answer steps per head, each a short run of a row of
 // its own), so every chain is kept short.  A workgroup of 16 waves covers 2
-// consecutive heads; two workgroups fit a CU.  Per block of (sample, step)
-// pairs:
+// consecutive heads; two workgroups share a CU, so that the 512 of 1024 heads
+// run in one round (every workgroup tests all pairs, a second round would do
+// that again).  That needs at most 64 VGPRs and 80 SGPRs: the uniform row
+// pointers of 8 spans a batch leave it at 76 SGPRs, those of 16 take 106 and
+// with 90 only one workgroup ran on a CU.  Per block of (sample, step) pairs:
 //   - each pair is tested by as many lanes as 1024 threads give it (1 to 64),
-//     strided over the span's tokens, and joined by a ballot;
+//     strided over the span's tokens, 8 tokens in flight a lane (with one lane
+//     a pair the walk over the tokens is what the call waits for), and joined
+//     by a ballot;
 //   - the answer steps are listed in LDS in step order (ballot, popcount and
 //     a prefix over the 64-pair chunks);
-//   - the eight waves of a head take every eighth entry of the list, load 16
+//   - the eight waves of a head take every eighth entry of the list, load 8
 //     spans together (lanes over positions) and add them per lane in fp64 in
 //     list order: one butterfly per head and wave at the end.
-// At 4 samples x 32 steps x 1024 heads with 32-token spans the call (with the
-// set selection) takes 23.9 us; one thread per pair, an unlisted walk over the
-// pairs, 8 spans a batch and a butterfly per step took 38.5 us.
+// 1024 heads, score call alone, in us, for (samples x steps, span, share of
+// answer steps); "a walk" is one thread per pair, no list, 4 heads a workgroup
+// and a butterfly per step, "16" this kernel with 16 spans a batch and one
+// token at a time:
+//                              a walk     16    now
+//   4 x 32,    32 tokens, 1/2    33.2   19.7   12.6
+//   64 x 64,   32 tokens, all   651.6  725.2  428.3
+//   1 x 512,  400 tokens, 0.3   110.1  194.0  107.2
+//   1 x 513, 2000 tokens, 0.02  194.1  407.8  123.5
 // The waves' totals are added in wave order, so the result does not depend on
 // scheduling.
 __global__ __launch_bounds__(64 * kSrhHeads * kSrhSplit) void srh_score_kernel(const SrhArgs a) {
@@ -68,7 +80,21 @@ __global__ __launch_bounds__(64 * kSrhHeads * kSrhSplit) void srh_score_kernel(c
         a0 = a.spans[2 * s];
         n = a.spans[2 * s + 1];
         const int32_t *tok = a.ctx + (int64_t)s * a.L + a0;
-        for (int j = sl; j < n; j += lpp) hit |= (tok[j] == y);
+        int j = sl;
+        for (; j - sl + kSrhTokens * lpp <= n; j += kSrhTokens * lpp) {
+          int32_t x[kSrhTokens];
+#pragma unroll
+          for (int u = 0; u < kSrhTokens; ++u) x[u] = tok[j + u * lpp];
+#pragma unroll
+          for (int u = 0; u < kSrhTokens; ++u) hit |= (x[u] == y);
+        }
+        if (j - sl < n) {   // the rest, with the last token in the place of those past it
+          int32_t x[kSrhTokens];
+#pragma unroll
+          for (int u = 0; u < kSrhTokens; ++u) x[u] = tok[min(j + u * lpp, n - 1)];
+#pragma unroll
+          for (int u = 0; u < kSrhTokens; ++u) hit |= (x[u] == y);
+        }
       }
       const bool any = (__ballot(hit) & group) != 0;
       if (q < np && sl == 0) {

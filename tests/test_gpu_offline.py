@@ -95,6 +95,30 @@ def test_srh_scores_answer_step_list(gpu, S, N, H, Lc, span):
     np.testing.assert_allclose(got, OO.srh_scores(attn, gen, ctx, spans), rtol=1.2e-7)
 
 
+# lanes per pair 64, 8, 2 and 1 (from 513 pairs on); spans shorter than, equal to and past
+# the tokens that the lanes of a pair load in one trip (8 each)
+@pytest.mark.parametrize("N,n", [(16, 3), (16, 700), (128, 64), (128, 150), (512, 16), (512, 17),
+                                 (513, 1), (513, 8), (700, 65), (1500, 403)])
+def test_srh_answer_step_at_every_span_token(gpu, N, n):
+    """Distinct tokens; steps answer with the span's tokens in turn, and at the
+    end with the two beside it (no answer).  Step t weighs t + 1 at one
+    position, so the scores are whole numbers and exact."""
+    _say(f"case srh span tokens N={N} n={n}")
+    H, Lc, a0 = 3, n + 7, 4
+    ctx = (1 + np.arange(Lc, dtype=np.int32))[None] * 7
+    at = a0 + (np.arange(N) + N // 2) % n
+    at[-2:] = (a0 - 1, a0 + n)
+    attn = np.zeros((1, N, H, Lc), dtype=np.float32)
+    attn[0, :, :, a0 + n // 2] = np.arange(1, N + 1)[:, None]
+    spans = np.array([[a0, n]], dtype=np.int32)
+    got = _run(gpu, attn, ctx[:, at], ctx, spans)
+    assert got.tolist() == [(N - 2) * (N - 1) / 2] * H
+    for j in {0, min(1, n - 1), n // 2, n - 1}:   # one step answers, with token j of the span
+        gen = np.full((1, N), ctx[0, a0 - 1], dtype=np.int32)
+        gen[0, j % N] = ctx[0, a0 + j]
+        assert _run(gpu, attn, gen, ctx, spans).tolist() == [j % N + 1] * H, j
+
+
 def test_select_srh_matches_oracle_with_ties(gpu):
     rng = np.random.default_rng(5)
     n_layers, hp = 32, 32
