@@ -39,8 +39,8 @@ typedef struct ckv_srh_problem {
  * attn       fp32 [S][N][H][L] dense: head h's attention weights at step t.
  * gen_tokens int32 [S][N]; ctx_tokens int32 [S][L]; spans int32 [S][2] (the
  *            device copy of spans_host).
- * scores     fp32 [H] (written).  Each head's sum runs in a fixed order: per
- *            step in fp32, over steps and samples in fp64.
+ * scores     fp32 [H] (written).  Every weight is added in fp64, in a fixed
+ *            order; each head's sum is rounded to fp32 once.
  */
 int compresskv_srh_scores(const ckv_srh_problem *p, const float *attn, const int32_t *gen_tokens,
                           const int32_t *ctx_tokens, const int32_t *spans, float *scores,
