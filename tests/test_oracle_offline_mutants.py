@@ -6,6 +6,7 @@ import numpy as np
 import pytest
 
 import oracle.offline_oracle as M
+from tests import test_gpu_offline as gpu_cases
 from tests import test_oracle_offline as pins
 
 
@@ -175,3 +176,30 @@ def test_pins_reject_offline_mutant(label, monkeypatch):
 def test_unmutated_offline_oracle_passes_all_pins():
     for pin in PINS:
         pin()
+
+
+# ------------------------------------ what the GPU cases of the eviction error can tell
+def _with_full(c, rows):
+    """The case with the cache rows `rows` as its full cache (the kept rows come first)."""
+    n_keep = int(c["idx"].max()) + 1
+    assert np.array_equal(rows[:n_keep], np.arange(n_keep))
+    return dict(c, k=c["k"][rows], v=c["v"][rows], cu=np.array([0, len(rows)], dtype=np.int32))
+
+
+def _tail_mutants(c):
+    """The last key of either cache left out, or counted twice."""
+    L = len(c["k"])
+    yield "full without its last key", _with_full(c, np.arange(L - 1))
+    yield "full with its last key twice", _with_full(c, np.append(np.arange(L), L - 1))
+    yield "compact without its last key", dict(c, idx=c["idx"][:, :, :-1])
+    yield "compact with its last key twice", dict(c, idx=np.append(c["idx"], c["idx"][:, :, -1:], 2))
+
+
+@pytest.mark.parametrize("T,L", sorted({(T, L) for _, _, T, L in gpu_cases.ROW_TILES}))
+def test_row_tile_cases_tell_a_tail_fault(T, L):
+    for D, dtype in sorted({(D, dt) for D, dt, _, _ in gpu_cases.ROW_TILES}):
+        c = gpu_cases._tail_case(D, dtype, T, L)
+        want = gpu_cases._oracle_error(c)
+        for label, m in _tail_mutants(c):
+            got = gpu_cases._oracle_error(m)
+            assert abs(got - want) > 100 * gpu_cases.ERR_RTOL * want, (label, D, dtype, got, want)
