@@ -261,6 +261,41 @@ def test_layer_error_row_tiles(gpu, D, dtype, T, L):
     np.testing.assert_allclose(_gpu_error(c, gpu), _oracle_error(c), rtol=ERR_RTOL)
 
 
+# 28 x 128 columns: three 64-column trips and two 16-column steps a wave, the W_O loads one
+# trip ahead; 8 to 32 vectors: one to four vector tiles; 40 rows of W_O: a workgroup of 8
+@pytest.mark.parametrize("dtype", [C.BF16, C.F32])
+@pytest.mark.parametrize("batch", [1, 2, 3, 4])
+def test_layer_error_projection_tiles(gpu, dtype, batch):
+    """Columns of W_O that only the trips' last and the 16-column steps reach
+    carry large weights, so that a trip left out or repeated shows."""
+    _say(f"case layer error projection dtype={dtype} batch={batch}")
+    c = _projection_case(dtype, batch)
+    np.testing.assert_allclose(_gpu_error(c, gpu), _oracle_error(c), rtol=ERR_RTOL)
+
+
+def _projection_case(dtype, batch):
+    c = _error_case(41, lens=(90, 70, 64, 33)[:batch], Hq=28, Hkv=4, D=128, T=8, B=20, d_model=40,
+                    dtype=dtype)
+    col = np.arange(28 * 128) % 224           # column of a wave's 224
+    c["w_o"][:, torch.from_numpy((col >= 128) & (col < 144))] *= 4.0
+    c["w_o"][:, torch.from_numpy(col >= 208)] *= 8.0
+    return c
+
+
+def _merge_case():
+    """1026 chunks in the full cache, one in the compact one; the keys of the
+    merge's second pass (chunks past 1024) carry the result."""
+    L = 1024 * 512 + 513
+    c = _error_case(42, lens=(L,), Hq=4, Hkv=1, D=64, T=1, B=40, d_model=32, dtype=C.BF16)
+    return _heavy_rows(c, lambda b, g: (1024 * 512, L - 1), 3000.0)
+
+
+def test_layer_error_merge_second_pass(gpu):
+    _say("case layer error merge second pass")
+    c = _merge_case()
+    np.testing.assert_allclose(_gpu_error(c, gpu), _oracle_error(c), rtol=ERR_RTOL)
+
+
 def test_layer_error_is_zero_when_every_position_is_kept(gpu):
     """B >= L: the compact cache holds every row in order, so both attentions
     see the same keys in the same chunks and the error is exactly 0."""

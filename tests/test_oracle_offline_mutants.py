@@ -203,3 +203,27 @@ def test_row_tile_cases_tell_a_tail_fault(T, L):
         for label, m in _tail_mutants(c):
             got = gpu_cases._oracle_error(m)
             assert abs(got - want) > 100 * gpu_cases.ERR_RTOL * want, (label, D, dtype, got, want)
+
+
+@pytest.mark.parametrize("batch", [1, 4])
+def test_projection_cases_tell_a_lost_trip(batch):
+    c = gpu_cases._projection_case(gpu_cases.C.F32, batch)
+    want = gpu_cases._oracle_error(c)
+    for first, last in ((128, 192), (192, 208), (208, 224)):   # a wave's last trip, its two steps
+        for factor in (0.0, 2.0):
+            w_o = c["w_o"].clone()
+            col = np.arange(w_o.shape[1]) % 224
+            w_o[:, (col >= first) & (col < last)] *= factor
+            got = gpu_cases._oracle_error(dict(c, w_o=w_o))
+            assert abs(got - want) > 100 * gpu_cases.ERR_RTOL * want, (first, factor, got, want)
+
+
+def test_merge_case_tells_a_lost_chunk():
+    c = gpu_cases._merge_case()
+    want = gpu_cases._oracle_error(c)
+    L, kept = len(c["k"]), c["idx"][0, 0]
+    assert kept.max() < 1024 * 512
+    for rows in (np.arange(1024 * 512), np.arange(L - 1),
+                 np.delete(np.arange(L), 1024 * 512)):
+        got = gpu_cases._oracle_error(_with_full(c, rows))
+        assert abs(got - want) > 100 * gpu_cases.ERR_RTOL * want, (len(rows), got, want)
