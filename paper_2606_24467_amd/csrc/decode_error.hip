@@ -90,12 +90,19 @@ __device__ __forceinline__ DecCache dec_cache(const DecArgs &a, int cache, int b
 // c) holds rows 4*quad .. +3 of a tile against columns CTW*c .. +CTW-1, so that
 // one LDS read gives its V elements of a key).
 //
-// A step is bound by its LDS accesses, so the rows are padded to spread over
-// the 64 banks: a logits row by 4 floats (16-byte accesses where a lane takes
-// consecutive keys; in P.V lane (quad, c) falls on bank 4 c + quad), a V row by
-// 16*CTW elements (the four quads' keys fall on banks of their own), and every
-// thread takes part in the softmax with its keys in registers.  One layer at
-// L = 32768, 32/8 heads, D = 128, bf16, 8 steps: the call 77.8 -> 76.2 us.
+// Bound by the chain of each 64-key step (logits, softmax and P.V, with a
+// barrier after each) at two workgroups a CU.  One layer at L = 32768, 32/8
+// heads, D = 128, bf16, 8 steps (42.7 us, 3.2 TB/s), counters: waves wait for
+// an issue slot in 50% of their cycles, for memory or a barrier in 24% and for
+// LDS in 3%; the matrix pipe, nearly all of it the fp32 P.V, is busy in 45% of
+// the SIMD cycles.  LDS rows are padded to spread over the 64 banks: a logits
+// row by 4 floats (16-byte accesses where a lane takes consecutive keys; in P.V
+// lane (quad, c) falls on bank 4 c + quad), a V row by 16*CTW elements (the
+// quads that one access serves together fall on banks of their own: all four,
+// or two of them where a lane reads 8 bytes, fp32 at D = 128).  That halved the
+// bank conflict cycles (2.97 -> 1.52 million), and the softmax keeps a thread's
+// keys in registers on as many threads as divide the rows (all 256, or 192 at
+// three row tiles); together the call went from 77.8 to 76.2 us.
 template <typename T, int D, int RT>
 __global__ __launch_bounds__(256) void dec_attn_kernel(const DecArgs a) {
   constexpr int NS = Slices<T, D>::n, U4 = QLayout<T, D>::U4, STRIDE = QLayout<T, D>::STRIDE;
@@ -197,8 +204,8 @@ __global__ __launch_bounds__(256) void dec_attn_kernel(const DecArgs a) {
     }
     if (k0 + kDecSub < c_end) issue(k0 + kDecSub);   // uniform
     __syncthreads();
-    // online softmax: TPR threads per row (as many as 256 threads give it), KPT
-    // consecutive keys each, held in registers
+    // online softmax: TPR threads per row (the largest power of two that 256
+    // threads give it), KPT consecutive keys each, held in registers
     {
       constexpr int TPR = RT == 1 ? 16 : (RT == 2 ? 8 : 4), KPT = kDecSub / TPR;
       const int r = tid / TPR, part = tid % TPR;
