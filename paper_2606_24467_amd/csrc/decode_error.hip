@@ -92,7 +92,7 @@ __device__ __forceinline__ DecCache dec_cache(const DecArgs &a, int cache, int b
 //
 // Bound by the chain of each 64-key step (logits, softmax and P.V, with a
 // barrier after each) at two workgroups a CU.  One layer at L = 32768, 32/8
-// heads, D = 128, bf16, 8 steps (42.7 us, 3.2 TB/s), counters: waves wait for
+// heads, D = 128, bf16, 8 steps (42.0 us, 3.2 TB/s), counters: waves wait for
 // an issue slot in 50% of their cycles, for memory or a barrier in 24% and for
 // LDS in 3%; the matrix pipe, nearly all of it the fp32 P.V, is busy in 45% of
 // the SIMD cycles.  LDS rows are padded to spread over the 64 banks: a logits

@@ -22,7 +22,7 @@ struct SrhArgs {
 
 constexpr int kSrhHeads = 2;        // heads per workgroup
 constexpr int kSrhSplit = 8;        // waves per head
-constexpr int kSrhBatch = 8;        // answer steps whose span loads a wave issues together
+constexpr int kSrhBatch = 4;        // answer steps whose span loads a wave issues together
 constexpr int kSrhTokens = 8;       // span tokens whose loads a lane of the test issues together
 constexpr int kSrhPairs = 2048;     // (sample, step) pairs tested per pass
 
@@ -31,26 +31,29 @@ constexpr int kSrhPairs = 2048;     // (sample, step) pairs tested per pass
 // consecutive heads; two workgroups share a CU, so that the 512 of 1024 heads
 // run in one round (every workgroup tests all pairs, a second round would do
 // that again).  That needs at most 64 VGPRs and 80 SGPRs: the uniform row
-// pointers of 8 spans a batch leave it at 76 SGPRs, those of 16 take 106 and
-// with 90 only one workgroup ran on a CU.  Per block of (sample, step) pairs:
+// pointers of 4 spans a batch leave it at 66 SGPRs, those of 8 take 90, and one
+// workgroup runs on a CU.  Per block of (sample, step) pairs:
 //   - each pair is tested by as many lanes as 1024 threads give it (1 to 64),
 //     strided over the span's tokens, 8 tokens in flight a lane (with one lane
 //     a pair the walk over the tokens is what the call waits for), and joined
 //     by a ballot;
 //   - the answer steps are listed in LDS in step order (ballot, popcount and
 //     a prefix over the 64-pair chunks);
-//   - the eight waves of a head take every eighth entry of the list, load 8
+//   - the eight waves of a head take every eighth entry of the list, load 4
 //     spans together (lanes over positions) and add them per lane in fp64 in
-//     list order: one butterfly per head and wave at the end.
-// 1024 heads, score call alone, in us, for (samples x steps, span, share of
-// answer steps); "a walk" is one thread per pair, no list, 4 heads a workgroup
-// and a butterfly per step, "16" this kernel with 16 spans a batch and one
-// token at a time:
-//                              a walk     16    now
-//   4 x 32,    32 tokens, 1/2    33.2   19.7   12.6
-//   64 x 64,   32 tokens, all   651.6  725.2  428.3
-//   1 x 512,  400 tokens, 0.3   110.1  194.0  107.2
-//   1 x 513, 2000 tokens, 0.02  194.1  407.8  123.5
+//     list order: one butterfly per head and wave at the end.  The loads are
+//     unconditional, past a span's end on its last position: guarded by the
+//     span's length, the compiler puts a load's conversion to fp64, and so the
+//     wait for it, before the next load.
+// Score call alone in us, for (samples x steps, heads, span, share of answer
+// steps); "walk" is one thread per pair, no list, 4 heads a workgroup and a
+// butterfly per step, "guarded" this kernel with 16 guarded loads a batch and
+// one token at a time:
+//                                     walk  guarded     now
+//   4 x 32,   1024,   32 tokens, 1/2    32.9     20.0    10.8
+//   64 x 64,  1024,   32 tokens, all   648.9    724.2   294.5
+//   1 x 512,  1024,  400 tokens, 0.3   110.2    194.1    67.4
+//   22 x 99,   448, 1611 tokens, 0.87 2072.5   3374.4  1337.1
 // The waves' totals are added in wave order, so the result does not depend on
 // scheduling.
 __global__ __launch_bounds__(64 * kSrhHeads * kSrhSplit) void srh_score_kernel(const SrhArgs a) {
@@ -129,7 +132,7 @@ __global__ __launch_bounds__(64 * kSrhHeads * kSrhSplit) void srh_score_kernel(c
         for (int b = 0; b < kSrhBatch; ++b) {
           const int i = i0 + kSrhSplit * b;
           const int q = __builtin_amdgcn_readfirstlane((int)list_s[min(i, nh - 1)]);
-          const int n = __builtin_amdgcn_readfirstlane(n_s[q]);
+          const int n = __builtin_amdgcn_readfirstlane(n_s[q]);   // >= 1: the list's entries
           const int a0 = __builtin_amdgcn_readfirstlane(a0_s[q]);
           len[b] = i < nh ? n : 0;
           row[b] = a.attn + ((int64_t)(p0 + q) * a.H + h) * (int64_t)a.L + a0;
@@ -139,9 +142,9 @@ __global__ __launch_bounds__(64 * kSrhHeads * kSrhSplit) void srh_score_kernel(c
           const int j = j0 + lane;
           float x[kSrhBatch];
 #pragma unroll
-          for (int b = 0; b < kSrhBatch; ++b) x[b] = (j < len[b]) ? row[b][j] : 0.f;
+          for (int b = 0; b < kSrhBatch; ++b) x[b] = row[b][min(j, max(len[b], 1) - 1)];
 #pragma unroll
-          for (int b = 0; b < kSrhBatch; ++b) acc += (double)x[b];
+          for (int b = 0; b < kSrhBatch; ++b) acc += (double)(j < len[b] ? x[b] : 0.f);
         }
       }
     }

@@ -1,5 +1,5 @@
-"""Registers and LDS that kernels may take, from the compiler's own output for
-gfx950 (no GPU needed)."""
+"""Registers and LDS that kernels may take and loads that they issue together,
+from the compiler's own output for gfx950 (no GPU needed)."""
 import os
 import re
 import subprocess
@@ -28,3 +28,18 @@ def test_two_srh_score_workgroups_fit_a_cu():
     assert vgprs + agprs <= 64
     assert scratch == 0
     assert 2 * lds <= 160 * 1024
+
+
+def test_srh_score_issues_a_batch_of_span_loads_together():
+    """Every span load of a batch is issued before the first one is waited for
+    and converted to fp64."""
+    src = os.path.join(B.CSRC, "offline.hip")
+    batch = int(re.search(r"kSrhBatch = (\d+);", open(src).read()).group(1))
+    r = subprocess.run([B._hipcc(), *B.FLAGS, "--cuda-device-only", "-S", src, "-o", "-"],
+                       capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-2000:]
+    body = re.search(r"^\S*srh_score_kernel\S*:(.*?)s_endpgm", r.stdout, re.S | re.M).group(1)
+    # back from the first conversion to the start of its run of straight-line code
+    before = body[:body.index("v_cvt_f64_f32")]
+    run = re.split(r"^(?:\S+:|\s+s_c?branch\S*|\s+s_\w*saveexec\S*)", before, flags=re.M)[-1]
+    assert len(re.findall(r"^\s+global_load_dword\s", run, re.M)) == batch
